@@ -90,7 +90,10 @@ typedef enum kred_status {
 #define KRED_FLAG_FAST 4u     /* D <= 4 (Gaussian sums and, at D <= 4, their x-gradient for a
                                  cotangent: D <= 16): use the matrix-core exponent whatever the
                                  problem size (the accuracy guard, c R^2 <= 256 for 4 < D <= 16,
-                                 still falls back to the direct form).  D > 16
+                                 still falls back to the direct form; without the flag the
+                                 cotangent's gradients and sums of more than 4 columns at D <= 3
+                                 are kept to smaller boxes, where they are as exact as the direct
+                                 form).  D > 16
                                  sums (and LSE at 17 <= D <= 128): the split bf16 products whatever
                                  the size (same guard).  D > 16
                                  arg-K-min: consider the exact bf16 kernel whatever the size (it

@@ -62,6 +62,8 @@ struct FastFrame {
 };
 // The decision (ok) is taken with this exact float arithmetic by the fast
 // kernels and by the direct-form kernels alike, so exactly one of them runs.
+// limit > 0 bounds c R^2; limit < 0 bounds the square of the largest half-width,
+// U^2 <= -limit.
 __device__ __forceinline__ FastFrame fast_frame(const FastGuard* g, int D, float scale, float limit) {
   FastFrame f;
   float r2 = 0.0f, U = 0.0f;
@@ -85,7 +87,7 @@ __device__ __forceinline__ FastFrame fast_frame(const FastGuard* g, int D, float
   }
   f.U = U;
   f.r2 = r2;
-  f.ok = r2 <= limit;   // false for NaN
+  f.ok = limit > 0.0f ? r2 <= limit : U * U <= -limit && r2 <= -limit * (float)D;   // false for NaN
   return f;
 }
 // Whether a call on the spatially ordered path orders its points: the fast
@@ -524,8 +526,14 @@ struct WideArgs {
 hipError_t launch_wide(const WideArgs& a, hipStream_t s);
 int wide_chunks(int D);
 int wide_dots(int Ec);
-// the largest c R^2 it takes (the bound in k_wide.hip)
-inline float wide_limit_box(int D) { return D <= 3 ? kFastLimit3 : 256.0f; }
+// The largest box it takes (see fast_frame).  KRED_FLAG_FAST: as far as the bound in
+// k_wide.hip goes.  By default: as far as it measures no less exact than the direct
+// form, whatever the signs of the weights (the figures are there).
+inline float wide_limit_box(int D, bool vjp, bool fast) {
+  if (!fast && vjp) return -24.0f;
+  if (!fast && D <= 3) return 512.0f;
+  return D <= 3 ? kFastLimit3 : 256.0f;
+}
 // counts[0] += 1 when the guard selects the fast path for (D, scale, limit),
 // counts[1] += 1 always: which kernel did the work, for the profile.
 hipError_t launch_fast_record(const FastGuard* g, int D, float scale, float limit, int* counts,

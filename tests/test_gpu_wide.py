@@ -116,3 +116,51 @@ def test_products_beyond_the_box_limit(ctx):
     assert ctx.profile_collect()[2] == "vjp_kernel"
     ref, norm = oracle.gauss_vjp(x, y, b, e, 0.005)
     assert norm_err(host(gx), ref, norm) <= SUM_TOL
+
+
+def _ratio(got, direct, ref):
+    """2-norm of the error against the direct form's."""
+    return np.linalg.norm(got - ref) / np.linalg.norm(direct - ref)
+
+
+# An error that is alike for all columns of a row does not average out as the
+# rounding of a long sum does, so the columns are many.  Both forms round every
+# term by a few 2^-24; 1.25 allows for the spread of two such errors over the rows.
+@pytest.mark.parametrize("D,E,sigma,kernel", [
+    (3, 3, 0.1, "wide_kernel"), (3, 16, 0.2, "wide_kernel"), (2, 3, 0.3, "wide_kernel"), (4, 8, 0.3, "wide_kernel"),
+    (2, 8, 0.1, "wide_kernel"), (3, 6, 0.05, "vjp_kernel"), (1, 6, 0.05, "vjp_kernel"),
+])
+@pytest.mark.parametrize("positive", [False, True])
+def test_products_are_as_exact_as_the_direct_form(ctx, D, E, sigma, kernel, positive):
+    rng = np.random.default_rng(D * 10 + E)
+    M, N = 2300, 120011                      # 2^28 pairs: the default takes the wide kernel
+    x = rng.uniform(0, 1, (M, D)).astype(np.float32)
+    y = rng.uniform(0, 1, (N, D)).astype(np.float32)
+    w = (lambda n: rng.uniform(0, 1, (n, E))) if positive else (lambda n: rng.standard_normal((n, E)))
+    b, e = w(N).astype(np.float32), w(M).astype(np.float32)
+    rows = np.arange(0, M, 9)
+    ref, _ = oracle.gauss_vjp(x, y, b, e, float(np.float32(sigma)), rows=rows)
+    dx, dy, db, de = dev(x), dev(y), dev(b), dev(e)
+    out = {}
+    for flags in (0, kred.FLAG_DIRECT):
+        ctx.profile_collect()
+        out[flags] = host(ctx.gauss_backward(dx, dy, db, de, sigma=sigma, gy=False, gb=False,
+                                             flags=flags | kred.FLAG_PROFILE)[0])[rows]
+        assert ctx.profile_collect()[2] == ("vjp_kernel" if flags else kernel)
+    assert _ratio(out[0], out[kred.FLAG_DIRECT], ref) <= 1.25
+
+
+@pytest.mark.parametrize("D,sigma", [(3, 0.1), (2, 0.1), (4, 0.2), (3, 0.02), (7, 0.6)])
+@pytest.mark.parametrize("positive", [False, True])
+def test_sums_are_as_exact_as_the_direct_form(ctx, D, sigma, positive):
+    rng = np.random.default_rng(D)
+    M, N, E = 600, 500009, 16
+    x = rng.uniform(0, 1, (M, D)).astype(np.float32)
+    y = rng.uniform(0, 1, (N, D)).astype(np.float32)
+    b = (rng.uniform(0, 1, (N, E)) if positive else rng.standard_normal((N, E))).astype(np.float32)
+    rows = np.arange(0, M, 6)
+    ref, _ = oracle.kernel_sum("gauss", x, y, b, sigma=float(np.float32(sigma)), rows=rows)
+    out = {}
+    for flags in (0, kred.FLAG_DIRECT):
+        out[flags] = host(ctx.run("gauss", "sum", dev(x), dev(y), dev(b), sigma=sigma, flags=flags))[rows]
+    assert _ratio(out[0], out[kred.FLAG_DIRECT], ref) <= 1.25
