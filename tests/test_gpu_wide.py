@@ -164,3 +164,19 @@ def test_sums_are_as_exact_as_the_direct_form(ctx, D, sigma, positive):
     for flags in (0, kred.FLAG_DIRECT):
         out[flags] = host(ctx.run("gauss", "sum", dev(x), dev(y), dev(b), sigma=sigma, flags=flags))[rows]
     assert _ratio(out[0], out[kred.FLAG_DIRECT], ref) <= 1.25
+
+
+@pytest.mark.parametrize("low", [-3.4028235e38, 3.4028235e38])
+def test_weights_of_the_types_largest_values(ctx, low):
+    """A head of three bf16 parts rounded to nearest would be infinite there."""
+    rng = np.random.default_rng(2)
+    x, y = rng.uniform(0, 1, (70, 3)).astype(np.float32), rng.uniform(0, 1, (300, 3)).astype(np.float32)
+    b = rng.standard_normal((300, 8)).astype(np.float32)
+    b[5, 3] = low
+    got = host(ctx.run("gauss", "sum", dev(x), dev(y), dev(b), sigma=0.4, flags=FAST))
+    ref, norm = oracle.kernel_sum("gauss", x, y, b, sigma=float(np.float32(0.4)))
+    assert norm_err(got, ref, norm) <= SUM_TOL
+    e = (rng.standard_normal((70, 8)) * 1e-3).astype(np.float32)
+    gx = host(ctx.gauss_backward(dev(x), dev(y), dev(b), dev(e), sigma=0.4, gy=False, gb=False, flags=FAST)[0])
+    ref, norm = oracle.gauss_vjp(x, y, b, e, float(np.float32(0.4)))
+    assert norm_err(gx, ref, norm) <= SUM_TOL
