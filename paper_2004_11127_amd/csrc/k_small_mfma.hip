@@ -84,12 +84,41 @@ __global__ void guard_init_kernel(FastGuard* g) {
   }
 }
 
+// The sample's quantiles along one coordinate, for the spatial order: 128 points of
+// each cloud, one from a pseudo-random place in each 128th of it, ranked by counting.
+__device__ __forceinline__ void sample_knots(const float* __restrict__ x, int64_t M,
+                                             const float* __restrict__ y, int64_t N, int D, int d,
+                                             float* sample, FastGuard* g) {
+  const int t = threadIdx.x;
+  const int64_t n = t < 128 ? M : N, at = n * (t & 127) / 128, len = n * ((t & 127) + 1) / 128 - at;
+  const int64_t i = min(at + (int64_t)((((unsigned)t + 1u) * 2654435761u) >> 8) % max(len, (int64_t)1), n - 1);
+  float v = (t < 128 ? x : y)[i * D + d];
+  if (v != v) v = 0.0f;
+  sample[t] = v;
+  __syncthreads();
+  int rank = 0;
+#pragma unroll 8
+  for (int u = 0; u < 256; ++u) {
+    const float o = sample[u];
+    rank += (o < v || (o == v && u < t)) ? 1 : 0;
+  }
+  if ((rank & 7) == 4) g->knot[d][rank >> 3] = v;
+}
+
 // Joint bounding box of x (M x D) and y (N x D): per-block reduction (wave
-// shuffles, then LDS), then one atomic per block and coordinate.
+// shuffles, then LDS), then one atomic per block and coordinate.  Blocks from nb
+// on take the sample's quantiles, one coordinate each.
 template <int MD>
 __global__ __launch_bounds__(256) void bounds_kernel(const float* __restrict__ x, int64_t M,
                                                      const float* __restrict__ y, int64_t N, int D,
-                                                     FastGuard* g) {
+                                                     int nb, FastGuard* g) {
+  if constexpr (MD <= kFastMaxD) {
+    __shared__ float sample[256];
+    if ((int)blockIdx.x >= nb) {
+      sample_knots(x, M, y, N, D, blockIdx.x - nb, sample, g);
+      return;
+    }
+  }
   __shared__ float red[2][MD][4];
   float lo[MD], hi[MD];
 #pragma unroll
@@ -97,7 +126,7 @@ __global__ __launch_bounds__(256) void bounds_kernel(const float* __restrict__ x
     lo[d] = __builtin_inff();
     hi[d] = -__builtin_inff();
   }
-  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
+  const int64_t stride = (int64_t)nb * blockDim.x;
   for (int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; t < M + N; t += stride) {
     const float* p = t < M ? x + t * D : y + (t - M) * D;
 #pragma unroll
@@ -148,7 +177,7 @@ __global__ __launch_bounds__(256) void fast_pack_kernel(FastPackArgs a) {
   const int64_t stride = (int64_t)gridDim.x * blockDim.x;
   const int* order = nullptr;
   if constexpr (SORT) {
-    if (4.0f * fr.r2 >= a.so.min_range) order = a.so.order_y;   // else in place (sort_useful)
+    if (a.guard->sorted) order = a.so.order_y;   // else in place
   }
   for (int64_t j = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; j < a.N16; j += stride) {
     __bf16 s[32];
@@ -225,7 +254,7 @@ __global__ __launch_bounds__(256) void fast_pack_kernel(FastPackArgs a) {
 
 // Box and weight bound of 64 subtiles: one wave each.
 __global__ __launch_bounds__(64) void super_box_kernel(FastPackArgs a) {
-  if (!fast_frame(a.guard, a.D, a.scale, a.limit).ok) return;
+  if (!a.guard->sorted) return;
   const int t = blockIdx.x * 64 + threadIdx.x;
   float4 lo = float4{__builtin_inff(), __builtin_inff(), __builtin_inff(), __builtin_inff()};
   float4 hi = float4{-__builtin_inff(), -__builtin_inff(), -__builtin_inff(), -__builtin_inff()};
@@ -336,10 +365,10 @@ void fast_kernel(FastArgs a) {
   __shared__ int Cn[SORT ? 4 : 1];
   __shared__ unsigned short Ls[SORT ? kSubChunk : 1];
 
+  // of a call that may order its points, one of the two variants does the work
+  if ((SORT || a.so.order_x != nullptr) && (a.guard->sorted != 0) != SORT) return;
   const FastFrame fr = fast_frame(a.guard, a.D, a.scale, a.limit);
   if (!fr.ok) return;
-  // with an order made, one of the two variants does the work (sort_useful)
-  if ((SORT || a.so.order_x != nullptr) && (4.0f * fr.r2 >= a.so.min_range) != SORT) return;
   const double qu = fast_quantum(fr.U);
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, li = lane & 15, g = lane >> 4;
@@ -1094,15 +1123,16 @@ void fast_kernel(FastArgs a) {
 int fast_rows_per_block(int epi, int K) { return (epi == FAST_KNN && K > 4) ? 64 * 2 : 64 * 4; }
 
 hipError_t launch_fast_bounds(const FastGuard* guard, const float* x, int64_t M, const float* y,
-                              int64_t N, int D, hipStream_t s) {
+                              int64_t N, int D, bool knots, hipStream_t s) {
   FastGuard* g = const_cast<FastGuard*>(guard);   // the prologue fills the guard
   hipLaunchKernelGGL(guard_init_kernel, dim3(1), dim3(64), 0, s, g);
   const int64_t items = M + N;
   const int64_t blocks = std::max<int64_t>(1, std::min<int64_t>((items + 255) / 256, 512));
   if (D <= kFastMaxD)
-    hipLaunchKernelGGL(bounds_kernel<kFastMaxD>, dim3((unsigned)blocks), dim3(256), 0, s, x, M, y, N, D, g);
+    hipLaunchKernelGGL(bounds_kernel<kFastMaxD>, dim3((unsigned)(blocks + (knots ? D : 0))), dim3(256), 0, s,
+                       x, M, y, N, D, (int)blocks, g);
   else
-    hipLaunchKernelGGL(bounds_kernel<kGuardMaxD>, dim3((unsigned)blocks), dim3(256), 0, s, x, M, y, N, D, g);
+    hipLaunchKernelGGL(bounds_kernel<kGuardMaxD>, dim3((unsigned)blocks), dim3(256), 0, s, x, M, y, N, D, (int)blocks, g);
   return hipGetLastError();
 }
 

@@ -41,9 +41,14 @@ inline float fast_limit(int D, bool nearest) {
 }
 
 constexpr int kGuardMaxD = 16;   // coordinates of the box (D <= 4: the fast path; D <= 16: k_wide.hip)
+constexpr int kKnots = 32;
 struct FastGuard {
   int lo[kGuardMaxD];   // order-preserving int encodings of the box corners
   int hi[kGuardMaxD];
+  // per coordinate, for the spatial order (D <= 4): quantiles (k + 1/2) / 32 of a
+  // sample of both clouds
+  float knot[4][kKnots];
+  int sorted;   // the points are ordered (sort_useful), set with the keys
 };
 
 __device__ __forceinline__ int fenc(float f) {
@@ -90,13 +95,25 @@ __device__ __forceinline__ FastFrame fast_frame(const FastGuard* g, int D, float
   f.ok = limit > 0.0f ? r2 <= limit : U * U <= -limit && r2 <= -limit * (float)D;   // false for NaN
   return f;
 }
+// Squared diagonal, in log2 units, of the clouds' bulk: along each coordinate the
+// span of 27 / 32 of the sample, scaled to the whole (a uniform cloud's box).  Some
+// far points stretch the box and not this.
+__device__ __forceinline__ float bulk_range(const FastGuard* g, int D, float scale) {
+  float r = 0.0f;
+  for (int d = 0; d < kFastMaxD; ++d)
+    if (d < D) {
+      const float h = (g->knot[d][29] - g->knot[d][2]) * (32.0f / 27.0f) * scale;
+      r = __builtin_fmaf(h, h, r);
+    }
+  return r;
+}
 // Whether a call on the spatially ordered path orders its points: the fast
-// path runs, and the box's diagonal spans at least min_range in log2 units
-// (below it no column tile could be left out, and the points stay in place).
+// path runs, and the bulk of the data spans at least min_range (below it no column
+// tile could be left out, and the points stay in place).  The keys' kernel decides,
+// and the others read the guard's flag.
 __device__ __forceinline__ bool sort_useful(const FastGuard* g, int D, float scale, float limit,
                                             float min_range) {
-  const FastFrame f = fast_frame(g, D, scale, limit);
-  return f.ok && 4.0f * f.r2 >= min_range;
+  return fast_frame(g, D, scale, limit).ok && bulk_range(g, D, scale) >= min_range;
 }
 
 // Prologue: copy y (and one E-slice of b) into a padded, prescaled,
@@ -397,7 +414,7 @@ struct SortArgs {
   const float* y;
   int64_t M, N;          // M + N < 2^30
   int D;
-  const FastGuard* guard;
+  FastGuard* guard;
   int always;                      // the order is always made
   float scale, limit, min_range;   // else when sort_useful
   // set by launch_sort, inside its scratch
@@ -459,9 +476,10 @@ struct FastPackArgs {
   int E;              // FAST_SUMV: signal columns of b (2..4)
   SortedCols so;      // ordered path: columns in the order's places, N16 a multiple of 64
 };
-// The box of both clouds into the guard; then the packed columns.
+// The box of both clouds into the guard (knots: and the sample's quantiles); then the
+// packed columns.
 hipError_t launch_fast_bounds(const FastGuard* guard, const float* x, int64_t M, const float* y,
-                              int64_t N, int D, hipStream_t s);
+                              int64_t N, int D, bool knots, hipStream_t s);
 hipError_t launch_fast_pack(const FastPackArgs& a, hipStream_t s);
 
 struct FastArgs {
