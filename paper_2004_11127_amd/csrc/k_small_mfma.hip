@@ -206,7 +206,7 @@ __global__ __launch_bounds__(256) void fast_pack_kernel(FastPackArgs a) {
     } else if constexpr (SORT) {
       s[kSlotW] = (__bf16)(nearest ? 0x1p100f : -0x1p100f);
     }
-    if constexpr (SORT) {
+    if (SORT && order != nullptr) {
       // the subtile's box, and its weight bound: log2 of sum_j |b_j| (of the
       // largest over the signal columns), or max_j g'_j + log2 64
       float lo[kFastMaxD], hi[kFastMaxD];

@@ -10,7 +10,13 @@
 // so equal keys keep their order and the result is the same on every run.
 // Both clouds go through the same launches (blocks of one cloud, then of the
 // other), and the first histogram is taken where the keys are made.  Latency
-// and launches bound it: 2 x 10^6 points take 145 us, 450 000 75 us.  (A
+// and launches bound it, so up to 2^17 points a cloud every scatter adds up the blocks
+// before its own by itself, and for the sums (the lists up to 2^15, at D <= 2 2^16) the keys
+// have 16 bits and two passes: four launches instead of nine.  us, nine launches and
+// four: 10 nearest of 6000 x 7000 points, D = 2 91 -> 72; of a mixture at D = 3, 32 000 x
+// 32 000 129 -> 117, at 65 000 181 -> 184 and at D = 4 258 -> 309 (too many points a cell); sum
+// of 10^5 x 10^5 whose order is of no use 1183 -> 1173.  (Histograms of the later passes by
+// atomics in the scatter before: 60 us slower at 200 000 points.)  (A
 // library sort would clear its counters with memory-set nodes, which a caller
 // that captures the reduction in a graph must not get.)
 #include "kred_internal.h"
@@ -20,7 +26,7 @@ namespace {
 
 constexpr int kSortBlock = 2048;              // points per workgroup
 constexpr int kSortRounds = kSortBlock / 256; // points per lane
-constexpr int kSortKeyBits = 24;
+constexpr int64_t kSortSmall = 131072;        // points a cloud of the short form
 
 // cell of one coordinate: floor of its share of the box, 24 / D bits
 __device__ __forceinline__ unsigned int cell_of(float v, float lo, float inv, int bits) {
@@ -145,7 +151,7 @@ __global__ __launch_bounds__(256) void sort_keys_kernel(SortArgs a) {
   __shared__ Axis ax[kFastMaxD];
   h[threadIdx.x] = 0;
   const SortBlock b = sort_block(a);
-  const int bits = kSortKeyBits / a.D;
+  const int bits = 8 * a.passes / a.D;
   if ((int)threadIdx.x < 32 * a.D) make_axis(a.guard, threadIdx.x >> 5, bits, &ax[threadIdx.x >> 5]);
   __syncthreads();
   const float* pts = b.cloud ? a.y : a.x;
@@ -239,7 +245,19 @@ __global__ __launch_bounds__(256) void sort_scatter_kernel(SortArgs a, const uns
     const int blk = b.cloud ? blockIdx.x - a.nbx : blockIdx.x;
     const int d = threadIdx.x;
     // the digits below d, then the earlier blocks' points of digit d
-    const int total = a.totals[256 * b.cloud + d];
+    const int* c = a.counts + (b.cloud ? (int64_t)256 * a.nbx : 0) + (int64_t)d * nb;
+    int total = 0, before = 0;
+    if (a.small) {
+#pragma unroll 8
+      for (int i = 0; i < nb; ++i) {
+        const int n = c[i];
+        total += n;
+        before += i < blk ? n : 0;
+      }
+    } else {
+      total = a.totals[256 * b.cloud + d];
+      before = c[blk];
+    }
     int s = total;
     for (int o = 1; o < 64; o <<= 1) {
       const int u = __shfl_up(s, o);
@@ -248,7 +266,7 @@ __global__ __launch_bounds__(256) void sort_scatter_kernel(SortArgs a, const uns
     if (lane == 63) tot[wave] = s;
     __syncthreads();
     for (int w = 0; w < wave; ++w) s += tot[w];
-    s += a.counts[(b.cloud ? (int64_t)256 * a.nbx : 0) + (int64_t)d * nb + blk] - total;
+    s += before - total;
 #pragma unroll
     for (int w = 0; w < 4; ++w) {
       const int n = base[w][d];
@@ -275,7 +293,7 @@ __global__ __launch_bounds__(256) void sort_scatter_kernel(SortArgs a, const uns
     if (ok && below == 0) base[wave][d] += __popcll(same);
     __builtin_amdgcn_wave_barrier();
     if (ok) {
-      if (key_out != nullptr) key_out[b.base + at] = k[r];
+      key_out[b.base + at] = k[r];
       idx_out[b.base + at] = v[r];
     }
   }
@@ -306,20 +324,24 @@ hipError_t launch_sort(SortArgs& a, void* scratch, hipStream_t s) {
   a.counts = reinterpret_cast<int*>(p + 4 * up(n * 4));
   a.totals = reinterpret_cast<int*>(p + 4 * up(n * 4) + up(nb * 256 * 4));
   a.key0 = k0;
+  a.small = a.M <= kSortSmall && a.N <= kSortSmall;
+  // (the lists, whose rows look at single cells, want fewer points in one)
+  a.passes = a.small && (!a.always || std::max(a.M, a.N) <= (a.D <= 2 ? 65536 : 32768)) ? 2 : 3;
   const dim3 grid((unsigned)nb), block(256);
   hipLaunchKernelGGL(sort_keys_kernel, grid, block, 0, s, a);
-  hipLaunchKernelGGL(sort_scan_kernel, dim3(512), block, 0, s, a);
-  hipLaunchKernelGGL(sort_scatter_kernel, grid, block, 0, s, a, k0, (const int*)nullptr, k1, i0, 0);
-  hipLaunchKernelGGL(sort_hist_kernel, grid, block, 0, s, a, k1, 8);
-  hipLaunchKernelGGL(sort_scan_kernel, dim3(512), block, 0, s, a);
-  hipLaunchKernelGGL(sort_scatter_kernel, grid, block, 0, s, a, k1, i0, k0, i1, 8);
-  hipLaunchKernelGGL(sort_hist_kernel, grid, block, 0, s, a, k0, 16);
-  hipLaunchKernelGGL(sort_scan_kernel, dim3(512), block, 0, s, a);
-  hipLaunchKernelGGL(sort_scatter_kernel, grid, block, 0, s, a, k0, i1, k1, i0, 16);
-  a.order_x = i0;
-  a.order_y = i0 + a.M;
-  a.keys_x = k1;
-  a.keys_y = k1 + a.M;
+  unsigned int* key[2] = {k0, k1};
+  int* idx[2] = {i1, i0};
+  for (int pass = 0; pass < a.passes; ++pass) {
+    if (pass > 0) hipLaunchKernelGGL(sort_hist_kernel, grid, block, 0, s, a, key[pass & 1], 8 * pass);
+    if (!a.small) hipLaunchKernelGGL(sort_scan_kernel, dim3(512), block, 0, s, a);
+    hipLaunchKernelGGL(sort_scatter_kernel, grid, block, 0, s, a, key[pass & 1],
+                       pass > 0 ? idx[pass & 1] : (const int*)nullptr, key[(pass + 1) & 1], idx[(pass + 1) & 1],
+                       8 * pass);
+  }
+  a.order_x = idx[a.passes & 1];
+  a.order_y = a.order_x + a.M;
+  a.keys_x = key[a.passes & 1];
+  a.keys_y = a.keys_x + a.M;
   return hipGetLastError();
 }
 

@@ -419,6 +419,7 @@ struct SortArgs {
   float scale, limit, min_range;   // else when sort_useful
   // set by launch_sort, inside its scratch
   int nbx, nby;
+  int passes, small;     // 8-bit passes; the scatters add up the blocks themselves
   int* counts;
   int* totals;           // points of each digit, by cloud
   unsigned int* key0;

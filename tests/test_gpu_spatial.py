@@ -248,3 +248,14 @@ def test_order_of_unevenly_spread_points(ctx, case):
     spread = [dev(x), dev(y)]
     t0, t1 = (_us(lambda: ctx.run("sqdist", "argkmin", *p, K=4)) for p in (plain, spread))
     assert t1 <= 7 * t0, (t1, t0)
+
+
+@pytest.mark.parametrize("M,N,D", [(32768, 32768, 3), (32769, 600, 4), (131072, 131072, 3), (131073, 700, 3),
+                                   (700, 131073, 1), (65536, 2049, 2), (65537, 2048, 2)])
+def test_lists_around_the_sorts_forms(ctx, M, N, D):
+    """Two and three passes, prefixes by the scatter and by a kernel of their own."""
+    rng = np.random.default_rng(M + N + D)
+    x = rng.integers(0, 50, (M, D)).astype(np.float32)
+    y = rng.integers(0, 50, (N, D)).astype(np.float32)
+    rows = _rows(rng, M)
+    assert np.array_equal(_lists(ctx, x, y, 12)[rows], oracle.argkmin(x, y, 12, rows=rows)[0])
