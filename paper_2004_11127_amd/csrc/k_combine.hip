@@ -140,6 +140,8 @@ __device__ __forceinline__ bool before(float d, int j, float d2, int j2) {
 // these groups 116 and 195.
 template <int KP, int G>
 __global__ __launch_bounds__(256) void combine_knn_kernel(CombineArgs a) {
+  if (redo_skip(a.redo)) return;
+  if (a.redo.rows != nullptr && a.guard != nullptr && !fast_frame(a.guard, a.D, a.fscale, a.flimit).ok) return;
   const int C = blocks_of(a);
   if (C == 1) return;
   const int q = threadIdx.x & (G - 1);

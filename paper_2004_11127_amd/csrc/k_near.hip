@@ -33,6 +33,7 @@ namespace {
 // a tie won.
 __global__ __launch_bounds__(256) void near_pack_kernel(NearArgs a) {
   const int64_t j = blockIdx.x * (int64_t)256 + threadIdx.x;   // a multiple of 64 columns
+  if (a.redo != nullptr && j < 2) a.redo[j] = 0;
   if (j >= (int64_t)a.so.nsub * kSubCols) return;
   const bool ok = j < a.N;
   const int i = ok ? a.so.order_y[j] : INT_MAX;
@@ -49,11 +50,15 @@ __global__ __launch_bounds__(256) void near_pack_kernel(NearArgs a) {
       hi[d] = fmaxf(hi[d], __shfl_xor(hi[d], o));
     }
   }
+  int low = i;
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) low = min(low, __shfl_xor(low, o));
   a.cols[j] = float4{v[0], v[1], v[2], a.D == 4 ? v[3] : __int_as_float(i)};
   if (a.D == 4) a.colj[j] = i;
   if ((threadIdx.x & 63) == 0) {
     a.so.box[2 * (j >> 6)] = float4{lo[0], lo[1], lo[2], lo[3]};
     a.so.box[2 * (j >> 6) + 1] = float4{hi[0], hi[1], hi[2], hi[3]};
+    a.low[j >> 6] = low;
   }
 }
 
@@ -106,9 +111,9 @@ __device__ __forceinline__ int from_below(int v) {
 }
 
 template <int D, int R>
-__global__ __launch_bounds__(64) void near_kernel(NearArgs a) {
+__device__ __forceinline__ void near_rows(const NearArgs& a, int wave, int budget) {
   const int lane = threadIdx.x;
-  const int64_t r0 = (int64_t)blockIdx.x * R;
+  const int64_t r0 = (int64_t)wave * R;
   const int rows = (int)min((int64_t)R, a.M - r0);
   const int K = a.K;
 
@@ -251,8 +256,8 @@ __global__ __launch_bounds__(64) void near_kernel(NearArgs a) {
     return b;
   };
 
-  // the rows' place among the columns: the last subtile whose first key is at
-  // most the middle row's (64 probes a step)
+  // the rows' place among the columns: the last subtile whose first key is below
+  // the middle row's (64 probes a step), so of equal columns the lowest come first
   const unsigned int key = a.so.keys_x[r0 + rows / 2];
   int p = 0;
   {
@@ -260,7 +265,7 @@ __global__ __launch_bounds__(64) void near_kernel(NearArgs a) {
     while (end - p > 1) {
       const int step = (end - p + 63) / 64;
       const int at = p + lane * step;
-      const bool le = at < end && a.so.keys_y[(int64_t)at * kSubCols] <= key;
+      const bool le = at < end && a.so.keys_y[(int64_t)at * kSubCols] < key;
       const int n = __popcll(__ballot(le));
       p += max(n - 1, 0) * step;
       end = min(p + step, end);
@@ -307,6 +312,14 @@ __global__ __launch_bounds__(64) void near_kernel(NearArgs a) {
           if (in) {
             load_box(a.so.box + 2 * id, bl, bh);
             d2 = gap2(bl, bh, lo, hi);
+            if (__builtin_expect(bound == 0.0f, 0)) {
+              // every row has K columns at its own place: only lower indices still
+              // count (a third of 250 000 points at one place: 4.8 ms without)
+              int top = 0;
+#pragma unroll
+              for (int r = 0; r < R; ++r) top = max(top, __builtin_amdgcn_readlane(lj[r], K - 1));
+              if (a.low[id] > top) d2 = __builtin_inff();
+            }
           }
           mt = __ballot(in);
           continue;
@@ -332,7 +345,14 @@ __global__ __launch_bounds__(64) void near_kernel(NearArgs a) {
   fetch(t1, cy[1], cj[1]);
   if (t1 >= 0) t2 = next(need[2]);
   fetch(t2, cy[2], cj[2]);
-  while (t1 >= 0) {
+  // A wave whose rows look at too many subtiles gives them up: after 64 if many of the
+  // boxes at hand still come as near as the K-th nearest, or after the budget.
+  int left = budget;
+  while (t1 >= 0 && left > 0) {
+    --left;
+    if (budget != INT_MAX && left == budget - 64 &&
+        4 * __popcll(__ballot(sd2 <= bound) & ms) > (R == 1 ? 3 : 1) * min(64, a.so.nsuper - (group - 1) * 64))
+      left = 0;
 #pragma unroll
     for (int d = 0; d < D; ++d) {
       cy[0][d] = cy[1][d];
@@ -349,6 +369,26 @@ __global__ __launch_bounds__(64) void near_kernel(NearArgs a) {
     visit();
     bound = farthest();
   }
+  if (t1 >= 0) {
+    // Rows lying apart (where the curve leaves a cluster) do better one at a time; one
+    // that three in four of the boxes come near to by itself has no use for the order.
+    const int id = (group - 1) * 64 + lane;
+    const bool in = id < a.so.nsuper;
+    float l[D], h[D];
+    load_box(a.so.sbox + 2 * (in ? id : 0), l, h);
+    int hopeless = 0;
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+      hopeless += 4 * __popcll(__ballot(in && gap2(l, h, xs[r], xs[r]) <= kth[r])) > 3 * __popcll(__ballot(in));
+    int at = 0;
+    if (lane == 0) {
+      if (hopeless > 0) atomicAdd(&a.redo[0], min(hopeless, rows));
+      at = atomicAdd(&a.redo[1], rows);
+    }
+    at = __builtin_amdgcn_readfirstlane(at);
+    if (lane < rows) a.redo[2 + at + lane] = (int)r0 + lane;
+    return;
+  }
 
 #pragma unroll
   for (int r = 0; r < R; ++r) {
@@ -361,21 +401,39 @@ __global__ __launch_bounds__(64) void near_kernel(NearArgs a) {
   }
 }
 
-}  // namespace
+template <int D, int R>
+__global__ __launch_bounds__(64) void near_kernel(NearArgs a) {
+  near_rows<D, R>(a, blockIdx.x, a.budget);
+}
 
-namespace {
-template <int R>
-hipError_t launch_near_rows(const NearArgs& a, hipStream_t s) {
-  const dim3 grid((unsigned)((a.M + R - 1) / R)), block(64);
-  switch (a.D) {
-    case 1: hipLaunchKernelGGL((near_kernel<1, R>), grid, block, 0, s, a); break;
-    case 2: hipLaunchKernelGGL((near_kernel<2, R>), grid, block, 0, s, a); break;
-    case 3: hipLaunchKernelGGL((near_kernel<3, R>), grid, block, 0, s, a); break;
-    case 4: hipLaunchKernelGGL((near_kernel<4, R>), grid, block, 0, s, a); break;
-    default: return hipErrorInvalidValue;
-  }
+// The rows given up, one at a time, unless the kernels behind do the call.
+template <int D>
+__global__ __launch_bounds__(64) void near_rest_kernel(NearArgs a) {
+  const int rows = a.redo[1];
+  if (rows == 0) return;
+  if (a.redo[0] >= a.from && (a.guard == nullptr || fast_frame(a.guard, a.D, 1.0f, a.limit).ok)) return;
+  for (int w = blockIdx.x; w < rows; w += gridDim.x) near_rows<D, 1>(a, a.redo[2 + w], INT_MAX);
+}
+
+template <int D, int R>
+hipError_t launch_near_as(const NearArgs& a, hipStream_t s) {
+  const unsigned waves = (unsigned)((a.M + R - 1) / R);
+  hipLaunchKernelGGL((near_kernel<D, R>), dim3(waves), dim3(64), 0, s, a);
+  if (a.redo != nullptr)
+    hipLaunchKernelGGL(near_rest_kernel<D>, dim3(std::min(waves, 4096u)), dim3(64), 0, s, a);
   return hipGetLastError();
 }
+template <int R>
+hipError_t launch_near_rows(const NearArgs& a, hipStream_t s) {
+  switch (a.D) {
+    case 1: return launch_near_as<1, R>(a, s);
+    case 2: return launch_near_as<2, R>(a, s);
+    case 3: return launch_near_as<3, R>(a, s);
+    case 4: return launch_near_as<4, R>(a, s);
+    default: return hipErrorInvalidValue;
+  }
+}
+
 }  // namespace
 
 hipError_t launch_near(const NearArgs& a, hipStream_t s) {

@@ -170,6 +170,7 @@ __global__ __launch_bounds__(256) void bounds_kernel(const float* __restrict__ x
 // or the distance 2^100).
 template <bool SORT>
 __global__ __launch_bounds__(256) void fast_pack_kernel(FastPackArgs a) {
+  if (redo_skip(a.redo)) return;
   const FastFrame fr = fast_frame(a.guard, a.D, a.scale, a.limit);
   if (!fr.ok) return;
   const double qu = fast_quantum(fr.U);
@@ -365,6 +366,9 @@ void fast_kernel(FastArgs a) {
   __shared__ int Cn[SORT ? 4 : 1];
   __shared__ unsigned short Ls[SORT ? kSubChunk : 1];
 
+  if constexpr (kMin || kKnn) {
+    if (redo_skip(a.redo)) return;
+  }
   // of a call that may order its points, one of the two variants does the work
   if ((SORT || a.so.order_x != nullptr) && (a.guard->sorted != 0) != SORT) return;
   const FastFrame fr = fast_frame(a.guard, a.D, a.scale, a.limit);

@@ -11,7 +11,7 @@
 // Both clouds go through the same launches (blocks of one cloud, then of the
 // other), and the first histogram is taken where the keys are made.  Latency
 // and launches bound it, so up to 2^17 points a cloud every scatter adds up the blocks
-// before its own by itself, and for the sums (the lists up to 2^15, at D <= 2 2^16) the keys
+// before its own by itself, and for the sums (the lists up to 2^16 at D <= 2, 2^15 at D = 3, 2^14 at D = 4) the keys
 // have 16 bits and two passes: four launches instead of nine.  us, nine launches and
 // four: 10 nearest of 6000 x 7000 points, D = 2 91 -> 72; of a mixture at D = 3, 32 000 x
 // 32 000 129 -> 117, at 65 000 181 -> 184 and at D = 4 258 -> 309 (too many points a cell); sum
@@ -79,8 +79,8 @@ __device__ __forceinline__ unsigned int hilbert_key(unsigned int (&q)[kFastMaxD]
 // linear between the sample's quantiles (and the box): monotone, so neighbours along
 // the axis stay neighbours.  Emptiness: the box's width times the integral of the
 // squared density, 1 for a uniform cloud, about 2.5 for a normal one, 8 where an
-// eighth of the cells would be filled; infinite where knots coincide (a lattice),
-// whose values the share of the points separates as well.
+// eighth of the cells would be filled.  (Coincident knots don't count: no grid
+// separates equal values.)
 struct Axis {
   float lo, inv;          // linear: offset and cells per unit
   float knot[kKnots + 2]; // box, quantiles, box
@@ -91,7 +91,8 @@ __device__ __forceinline__ void make_axis(const FastGuard* g, int d, int bits, A
   const int k = threadIdx.x & 31;
   const float lo = fdec(g->lo[d]), hi = fdec(g->hi[d]), w = hi - lo;
   const float q = g->knot[d][k];
-  float s = k < kKnots - 1 ? 1.0f / (g->knot[d][k + 1] - q) : 0.0f;
+  const float len = k < kKnots - 1 ? g->knot[d][k + 1] - q : 0.0f;
+  float s = len > 0.0f ? 1.0f / len : 0.0f;
   for (int o = 16; o > 0; o >>= 1) s += __shfl_xor(s, o, 32);
   ax->knot[k + 1] = fminf(fmaxf(q, lo), hi);
   if (k == 0) {
@@ -326,7 +327,7 @@ hipError_t launch_sort(SortArgs& a, void* scratch, hipStream_t s) {
   a.key0 = k0;
   a.small = a.M <= kSortSmall && a.N <= kSortSmall;
   // (the lists, whose rows look at single cells, want fewer points in one)
-  a.passes = a.small && (!a.always || std::max(a.M, a.N) <= (a.D <= 2 ? 65536 : 32768)) ? 2 : 3;
+  a.passes = a.small && (!a.always || std::max(a.M, a.N) <= (a.D <= 2 ? 65536 : a.D == 3 ? 32768 : 16384)) ? 2 : 3;
   const dim3 grid((unsigned)nb), block(256);
   hipLaunchKernelGGL(sort_keys_kernel, grid, block, 0, s, a);
   unsigned int* key[2] = {k0, k1};

@@ -116,6 +116,16 @@ __device__ __forceinline__ bool sort_useful(const FastGuard* g, int D, float sca
   return fast_frame(g, D, scale, limit).ok && bulk_range(g, D, scale) >= min_range;
 }
 
+// The neighbour lists (k_near.hip) count the rows that their order does not help in
+// rows[0] (rows[1] are given up and listed from rows[2] on).  From `from` of them on the
+// kernels that visit every pair, launched behind with a Redo, do the whole call; below,
+// the lists finish the rows given up.
+struct Redo {
+  const int* rows;   // null: an ordinary call
+  int from;
+};
+__device__ __forceinline__ bool redo_skip(const Redo& r) { return r.rows != nullptr && r.rows[0] < r.from; }
+
 // Prologue: copy y (and one E-slice of b) into a padded, prescaled,
 // interleaved array ypk[j * S + s], S = DP + EP:
 //   s <  D        : y[j, s] * yscale
@@ -133,6 +143,7 @@ struct PackArgs {
   float fscale;             // prescale of the fast path (for its guard test)
   float flimit;             // the fast path's limit on c R^2 (for its guard test)
   int unit_b;               // b == null: the signal column is bscale (a constant 1 * sign)
+  Redo redo;                // arg-K-min lists: whether to do anything
 };
 hipError_t launch_pack(const PackArgs& a, hipStream_t s);
 
@@ -170,6 +181,7 @@ struct DirectArgs {
   const int* cp;
   const int* cr;
   const int* bstart;
+  Redo redo;              // arg-K-min lists: whether to do anything
 };
 hipError_t launch_direct(const DirectArgs& a, hipStream_t s);
 // bstart[0..nr]: prefix sums of ceil(cluster rows / rows_per_block) (one workgroup).
@@ -214,6 +226,7 @@ struct CombineArgs {
   const FastGuard* guard;
   float fscale, flimit;
   int fast_C;
+  Redo redo;        // arg-K-min lists: whether to do anything (with a guard: and if the fast kernel ran)
 };
 hipError_t launch_combine(const CombineArgs& a, hipStream_t s);
 
@@ -459,6 +472,12 @@ struct NearArgs {
   int* colj;             // their indices (D = 4)
   SortedCols so;
   void* out;             // M x K
+  int* low;              // the lowest column index of every subtile
+  int* redo;             // null, or the rows given up (see Redo) after
+  int budget;            // this many subtiles
+  int from;              // Redo::from, and what else the kernels behind need to run
+  const FastGuard* guard;
+  float limit;
 };
 hipError_t launch_near(const NearArgs& a, hipStream_t s);
 
@@ -476,6 +495,7 @@ struct FastPackArgs {
   float* eb;          // sum: b per column
   int E;              // FAST_SUMV: signal columns of b (2..4)
   SortedCols so;      // ordered path: columns in the order's places, N16 a multiple of 64
+  Redo redo;          // FAST_MIN, FAST_KNN: whether to do anything
 };
 // The box of both clouds into the guard (knots: and the sample's quantiles); then the
 // packed columns.
@@ -503,6 +523,7 @@ struct FastArgs {
   const float* y;     // FAST_MIN, FAST_KNN: the points (N x D), for the exact final distances
   int E, EP;          // FAST_SUMV: signal columns, and the partial width of the sums' combine
   SortedCols so;      // the ordered path (so.order_x non-null; dense calls only)
+  Redo redo;          // FAST_MIN, FAST_KNN: whether to do anything
   // block-sparse pattern (nr > 0), as in DirectArgs; bstart counts row
   // blocks of fast_rows_per_block rows
   int nr;

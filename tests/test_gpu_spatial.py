@@ -13,7 +13,7 @@ import numpy as np
 import pytest
 
 import oracle
-from helpers import LSE_TOL, SUM_TOL, dev, host, lse_err, norm_err
+from helpers import LSE_TOL, SUM_TOL, dev, fast_limit, host, lse_err, norm_err
 from paper_2004_11127_amd import kred
 
 pytestmark = pytest.mark.gpu
@@ -107,17 +107,50 @@ def _clouds(rng, M, N, D, data):
     return x.astype(np.float32), y.astype(np.float32)
 
 
+def _bulk(x, y, d):
+    """The span of 27 / 32 of the device's sample along d, scaled to the whole: 128 points of each cloud, one
+    from a pseudo-random place in each 128th."""
+    v = []
+    for p in (x, y):
+        for u in range(128):
+            t, n = u + (128 if p is y else 0), len(p)
+            at, end = n * u // 128, n * (u + 1) // 128
+            v.append(p[min(at + (((t + 1) * 2654435761 & 0xFFFFFFFF) >> 8) % max(end - at, 1), n - 1), d])
+    q = np.sort(np.array(v))[4::8]
+    return float(q[29] - q[2]) * 32 / 27
+
+
+def _ordered(x, y, c):
+    """Whether a sum with exponent -c |x - y|^2 (log2 units) takes the ordered kernel: the matrix-core path's box
+    limit holds, and the clouds' bulk spans more than the rule asks at these sizes."""
+    (M, D), N = x.shape, len(y)
+    half = (np.maximum(x.max(0), y.max(0)) - np.minimum(x.min(0), y.min(0))) / 2
+    f = (256 / M) ** (1 / D) + (64 / N) ** (1 / D)
+    return (M * N >= 1e10 and f < 0.6 and c * (half ** 2).sum() <= fast_limit(D, False)
+            and c * sum(_bulk(x, y, d) ** 2 for d in range(D)) >= 45 / (0.6 - f) ** 2)
+
+
+def test_far_points_do_not_make_an_order_useful():
+    rng = np.random.default_rng(1)
+    x, y = rng.uniform(0, 1, (2, 100000, 3)).astype(np.float32)
+    c = 1.4426950408889634 / (2 * 0.2 ** 2)
+    assert not _ordered(x, y, c) and _ordered(x, y, 16 * c)
+    x[5] = 6
+    assert not _ordered(x, y, c)
+
+
 @pytest.mark.parametrize("formula,E", [("gauss", 1), ("gauss", 3), ("gauss_gradx", 1), ("sinkhorn", 1)])
 @pytest.mark.parametrize("M,N,D,data,sigma", [
     (100001, 100130, 3, "mixture", 0.05), (100000, 100064, 2, "uniform", 0.02), (40001, 262144 + 4097, 3, "uniform", 0.03),
-    (300001, 40961, 1, "uniform", 0.01), (120007, 90001, 4, "mixture", 0.2),
+    (300001, 40961, 1, "uniform", 0.012), (1000003, 1000100, 4, "uniform", 0.092),
 ])
 def test_ordered_sums(ctx, formula, E, M, N, D, data, sigma):
     if formula == "gauss_gradx" and D == 4:
         pytest.skip("the fused gradient's fast path has D <= 3")
     rng = np.random.default_rng(M)
     x, y = _clouds(rng, M, N, D, data)
-    x[7] = 1.9                                   # a row far from its neighbours on the curve
+    x[7] = 1.2                                   # a row far from its neighbours on the curve
+    assert _ordered(x, y, 1.4426950408889634 / (2 * sigma * sigma))
     b = rng.standard_normal((N, E)).astype(np.float32)
     b[np.linalg.norm(y - x[11], axis=1) < 2 * sigma] = 0      # a row whose near sum is zero
     red = "lse" if formula == "sinkhorn" else "sum"
@@ -129,7 +162,11 @@ def test_ordered_sums(ctx, formula, E, M, N, D, data, sigma):
     if formula == "sinkhorn":
         ref, m = oracle.sinkhorn_lse(x, y, b, kw["eps"], rows=rows)
         assert lse_err(got[rows], ref, m) <= LSE_TOL
-        assert np.abs(got - place).max() <= 2e-5
+        # the exponent's error bound, 1.2e-4 log2 units on either side at c R^2 = 2048 (the
+        # reference enters the two calls' products at different values), in proportion
+        half = (np.maximum(x.max(0), y.max(0)) - np.minimum(x.min(0), y.min(0))) / 2
+        L = 1.4426950408889634 / (2 * sigma * sigma) * float((half ** 2).sum())
+        assert np.abs(got - place).max() <= 2e-5 + 2 * 1.2e-4 * np.log(2) * L / 2048
         return
     if formula == "gauss_gradx":
         a, g, norm, _ = _gradx(x, y, b, sigma, rows)
@@ -164,15 +201,34 @@ def test_ordered_log_sums_of_masked_columns(ctx, low):
     assert lse_err(got[rows], ref, m) <= LSE_TOL
 
 
-def test_small_scratch_runs_in_place(ctx):
-    """The no-allocation entry point keeps taking calls whose scratch has no room for the order."""
+# with the order and the all-pairs kernels' scratch behind it, the order
+# alone (the kernels behind pack 100 bytes a column), points in place (more rows than the
+# order has room for)
+@pytest.mark.parametrize("M,N,K,fits", [(1500, 20000, 4, True), (1500, 300000, 10, False), (2200000, 3000, 4, False),
+                                        (2200000, 3000, 1, False)])
+def test_small_scratch_lists(ctx, M, N, K, fits):
+    """The no-allocation entry point keeps taking calls whose scratch has no room for all of the order's."""
     rng = np.random.default_rng(6)
-    x = rng.integers(0, 20, (600000, 3)).astype(np.float32)
-    y = rng.integers(0, 20, (30000, 3)).astype(np.float32)
-    sort = kred.scratch_bytes("sqdist", "argkmin", 600000, 30000, 3, 0, K=4)
-    got = host(ctx.run_noalloc("sqdist", "argkmin", dev(x), dev(y), K=4))
-    rows = _rows(rng, 600000)
-    assert sort > 0 and np.array_equal(got[rows], oracle.argkmin(x, y, 4, rows=rows)[0])
+    x = rng.integers(0, 20, (M, 3)).astype(np.float32)
+    y = rng.integers(0, 20, (N, 3)).astype(np.float32)
+    need = kred.scratch_bytes("sqdist", "argkmin", M, N, 3, 0, K=K)
+    assert (need < kred.NOALLOC_SCRATCH_BYTES - (1 << 20)) == fits
+    got = host(ctx.run_noalloc("sqdist", "argkmin", dev(x), dev(y), K=K))
+    rows = _rows(rng, M)
+    assert np.array_equal(got[rows], oracle.argkmin(x, y, K, rows=rows)[0])
+
+
+# the order (D = 3) and the 32x32-tile operands (D = 10) do not fit, the form without them does
+@pytest.mark.parametrize("M,N,D,sigma", [(2200000, 5000, 3, 0.05), (300000, 20000, 10, 2.5)])
+def test_small_scratch_sums(ctx, M, N, D, sigma):
+    rng = np.random.default_rng(7)
+    x, y = _clouds(rng, M, N, D, "mixture")
+    b = rng.standard_normal((N, 1)).astype(np.float32)
+    assert kred.scratch_bytes("gauss", "sum", M, N, D, 1, sigma=sigma) > kred.NOALLOC_SCRATCH_BYTES
+    got = host(ctx.run_noalloc("gauss", "sum", dev(x), dev(y), dev(b), sigma=sigma))
+    rows = _rows(rng, M, 64)
+    ref, norm = oracle.kernel_sum("gauss", x, y, b, sigma=sigma, rows=rows)
+    assert norm_err(got[rows], ref, norm) <= SUM_TOL
 
 
 def test_order_repeats_under_graph_replay(ctx):
@@ -259,3 +315,67 @@ def test_lists_around_the_sorts_forms(ctx, M, N, D):
     y = rng.integers(0, 50, (N, D)).astype(np.float32)
     rows = _rows(rng, M)
     assert np.array_equal(_lists(ctx, x, y, 12)[rows], oracle.argkmin(x, y, 12, rows=rows)[0])
+
+
+def _shell(rng, N, top):
+    """Integer points at one distance of the origin (many times each)."""
+    g = np.arange(-top, top + 1)
+    v = np.stack(np.meshgrid(g, g, g, indexing="ij"), -1).reshape(-1, 3)
+    n = (v ** 2).sum(1)
+    best = max(set(n.tolist()), key=lambda s: (n == s).sum())
+    v = v[n == best]
+    return v[rng.integers(0, len(v), N)].astype(np.float32)
+
+
+# rows inside a shell of columns: the order cannot keep any column out, and the rows
+# are left to the kernels that visit every pair (both row-block sizes, with and without
+# a second pass; sparse rows of that kind among others; K beyond 16 stays)
+@pytest.mark.parametrize("M,N,K,scale,some", [
+    (16384, 20000, 1, 1, False), (16500, 20001, 10, 1, False), (16500, 20001, 4, 1, True), (3000, 20000, 10, 1, False),
+    (16500, 20001, 16, 1, True), (16500, 20001, 10, 60, False), (140001, 9000, 10, 1, True), (2100, 20000, 30, 1, False),
+    (700001, 8300, 2, 1, True), (16500, 20001, 1, 60, True),
+])
+@pytest.mark.parametrize("reduction", ["argkmin", "kmin"])
+def test_lists_that_the_order_does_not_help(ctx, M, N, K, scale, some, reduction):
+    rng = np.random.default_rng(M + K)
+    y = _shell(rng, N, 12) * scale
+    x = rng.integers(-1, 2, (M, 3)).astype(np.float32) * scale
+    if some:
+        x[np.arange(M) % 977 != 5] += np.float32(9 * scale)
+    rows = np.unique(np.concatenate([_rows(rng, M), np.arange(5, M, 977)[:40]]))
+    got = _lists(ctx, x, y, K, reduction)[rows]
+    want, d = oracle.argkmin(x, y, K, rows=rows)
+    assert np.array_equal(got, want if reduction == "argkmin" else d.astype(np.float32))
+
+
+@pytest.mark.parametrize("M,N,K", [(16500, 20001, 10), (40000, 30011, 1), (3000, 20000, 40)])
+def test_lists_of_many_equal_points(ctx, M, N, K):
+    """A third of both clouds at one place (padding): the lowest indices of it, whatever the order."""
+    rng = np.random.default_rng(M)
+    x = rng.integers(0, 60, (M, 3)).astype(np.float32)
+    y = rng.integers(0, 60, (N, 3)).astype(np.float32)
+    x[::3] = 7
+    y[1::3] = 7
+    rows = _rows(rng, M)
+    assert np.array_equal(_lists(ctx, x, y, K)[rows], oracle.argkmin(x, y, K, rows=rows)[0])
+    assert np.array_equal(_lists(ctx, x, y, K)[3], np.arange(N)[(y == 7).all(1)][:K])
+
+
+def test_time_of_lists_that_the_order_does_not_help(ctx):
+    """Not far behind the kernels that visit every pair (which the flag selects), nor where many
+    points coincide.  Measured 1.15 times; 6 times when such rows were finished over the order."""
+    rng = np.random.default_rng(4)
+    s = rng.standard_normal((100000, 3))
+    y = dev((s / np.linalg.norm(s, axis=1, keepdims=True)).astype(np.float32))
+    x = dev((1e-4 * rng.uniform(0, 1, (100000, 3))).astype(np.float32))
+    run = lambda flags: _us(lambda: ctx.run("sqdist", "argkmin", x, y, K=1, flags=flags))
+    t0, t1 = run(kred.FLAG_FAST), run(0)
+    assert t1 <= 2 * t0, (t1, t0)
+    x, y = _clouds(rng, 100000, 100000, 3, "mixture")
+    px, py = dev(x), dev(y)
+    plain = _us(lambda: ctx.run("sqdist", "argkmin", px, py, K=10))
+    x[::3] = 3
+    y[::3] = 3
+    px, py = dev(x), dev(y)
+    t2 = _us(lambda: ctx.run("sqdist", "argkmin", px, py, K=10))
+    assert t2 <= 2 * plain, (t2, plain)
