@@ -289,9 +289,13 @@ __global__ __launch_bounds__(256) void sort_scatter_kernel(SortArgs a, const uns
     const int below = __popcll(same & ((1ull << lane) - 1ull));
     int at = 0;
     if (ok) at = base[wave][d] + below;
-    // the digit's first lane moves the wave's place on, after every lane read it
+    // the digit's first lane moves the wave's place on, after every lane read it (the
+    // fences order the lanes' accesses; a wave's LDS operations run in order, so they
+    // cost nothing)
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     __builtin_amdgcn_wave_barrier();
     if (ok && below == 0) base[wave][d] += __popcll(same);
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     __builtin_amdgcn_wave_barrier();
     if (ok) {
       key_out[b.base + at] = k[r];
