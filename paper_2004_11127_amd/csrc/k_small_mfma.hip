@@ -166,8 +166,8 @@ __global__ __launch_bounds__(256) void bounds_kernel(const float* __restrict__ x
 //
 // SORT: place j takes the order's j-th column, N16 is a multiple of 64 and a
 // wave packs one subtile at a time, so its box and weight bound are wave
-// reductions; a padding column's norm slot removes it (the exponent -2^100,
-// or the distance 2^100).
+// reductions; a padding column's norm slot removes it (the exponent -2^100).  The
+// nearest forms have no ordered variant.
 template <bool SORT>
 __global__ __launch_bounds__(256) void fast_pack_kernel(FastPackArgs a) {
   if (redo_skip(a.redo)) return;
@@ -205,7 +205,7 @@ __global__ __launch_bounds__(256) void fast_pack_kernel(FastPackArgs a) {
         ex.x = bj;
       }
     } else if constexpr (SORT) {
-      s[kSlotW] = (__bf16)(nearest ? 0x1p100f : -0x1p100f);
+      s[kSlotW] = (__bf16)-0x1p100f;
     }
     if (SORT && order != nullptr) {
       // the subtile's box, and its weight bound: log2 of sum_j |b_j| (of the
@@ -227,7 +227,7 @@ __global__ __launch_bounds__(256) void fast_pack_kernel(FastPackArgs a) {
         w = g2f;
         for (int o = 32; o > 0; o >>= 1) w = fmaxf(w, __shfl_xor(w, o));
         w += 6.0f;
-      } else if (!nearest) {
+      } else {
         float b4[4] = {fabsf(ex.x), a.epi == FAST_SUMV ? fabsf(ex.y) : 0.0f,
                        a.epi == FAST_SUMV ? fabsf(ex.z) : 0.0f, a.epi == FAST_SUMV ? fabsf(ex.w) : 0.0f};
 #pragma unroll
@@ -991,11 +991,11 @@ void fast_kernel(FastArgs a) {
   // indexed by constants only
   if constexpr (kKnn) {
     static_assert(RB == 2 || RB == 4, "the K-nearest epilogue runs 2 or 4 row blocks per wave");
-    knn_out(dk[0], jk[0], row_of(i0 + li), i0 + li < row_end);
-    knn_out(dk[1], jk[1], row_of(i0 + 16 + li), i0 + 16 + li < row_end);
+    knn_out(dk[0], jk[0], i0 + li, i0 + li < row_end);
+    knn_out(dk[1], jk[1], i0 + 16 + li, i0 + 16 + li < row_end);
     if constexpr (RB == 4) {
-      knn_out(dk[RB > 2 ? 2 : 0], jk[RB > 2 ? 2 : 0], row_of(i0 + 32 + li), i0 + 32 + li < row_end);
-      knn_out(dk[RB > 3 ? 3 : 0], jk[RB > 3 ? 3 : 0], row_of(i0 + 48 + li), i0 + 48 + li < row_end);
+      knn_out(dk[RB > 2 ? 2 : 0], jk[RB > 2 ? 2 : 0], i0 + 32 + li, i0 + 32 + li < row_end);
+      knn_out(dk[RB > 3 ? 3 : 0], jk[RB > 3 ? 3 : 0], i0 + 48 + li, i0 + 48 + li < row_end);
     }
   }
 

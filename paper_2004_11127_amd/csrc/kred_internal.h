@@ -451,14 +451,13 @@ constexpr int kSubCols = 64;
 struct SortedCols {
   const int* order_x;    // null: the unordered path
   const int* order_y;
-  const unsigned int* keys_x;
+  const unsigned int* keys_x;   // (the neighbour lists)
   const unsigned int* keys_y;
   float4* box;           // 2 per subtile
   float* lw;
   float4* sbox;          // 2 per 64 subtiles
   float* slw;
   int nsub, nsuper;
-  float min_range;       // of sort_useful
 };
 
 // The K nearest columns of every row over the ordered clouds (k_near.hip).
