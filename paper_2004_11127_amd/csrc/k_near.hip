@@ -20,7 +20,7 @@
 // a shift by one lane whatever K is (64 nearest of 200 003 x 250 000: 172 -> 1.0
 // ms), and the test that keeps columns out uses the exact K-th distance.  Equal distances keep the lower index, whatever the
 // order the columns come in.
-#include "kred_internal.h"
+#include "k_fast_slots.h"
 
 #include <cfloat>
 #include <climits>
@@ -406,12 +406,31 @@ __global__ __launch_bounds__(64) void near_kernel(NearArgs a) {
   near_rows<D, R>(a, blockIdx.x, a.budget);
 }
 
-// The rows given up, one at a time, unless the kernels behind do the call.
+// The rows given up, one at a time; or, if the kernels behind do the call, the columns
+// for the fast kernel (in the place of the lists' own scratch).
 template <int D>
 __global__ __launch_bounds__(64) void near_rest_kernel(NearArgs a) {
   const int rows = a.redo[1];
   if (rows == 0) return;
-  if (a.redo[0] >= a.from && (a.guard == nullptr || fast_frame(a.guard, a.D, 1.0f, a.limit).ok)) return;
+  if (a.redo[0] >= a.from) {
+    if (a.guard == nullptr) return;
+    const FastFrame fr = fast_frame(a.guard, a.D, 1.0f, a.limit);
+    if (fr.ok) {
+      const double qu = fast_quantum(fr.U);
+      for (int64_t j = blockIdx.x * (int64_t)64 + threadIdx.x; j < a.N16; j += (int64_t)gridDim.x * 64) {
+        __bf16 s[32];
+#pragma unroll
+        for (int k = 0; k < 32; ++k) s[k] = (__bf16)0.0f;
+        float vt[kFastMaxD];
+        if (j < a.N) pack_column<D == 4>(a.y, D, 1.0, fr, qu, j, true, 0.0, s, vt);
+        uint4 w[4];
+        __builtin_memcpy(w, s, 64);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) a.apk[j * 4 + q] = w[q];
+      }
+      return;
+    }
+  }
   for (int w = blockIdx.x; w < rows; w += gridDim.x) near_rows<D, 1>(a, a.redo[2 + w], INT_MAX);
 }
 

@@ -170,7 +170,6 @@ __global__ __launch_bounds__(256) void bounds_kernel(const float* __restrict__ x
 // nearest forms have no ordered variant.
 template <bool SORT>
 __global__ __launch_bounds__(256) void fast_pack_kernel(FastPackArgs a) {
-  if (redo_skip(a.redo)) return;
   const FastFrame fr = fast_frame(a.guard, a.D, a.scale, a.limit);
   if (!fr.ok) return;
   const double qu = fast_quantum(fr.U);

@@ -474,9 +474,11 @@ struct NearArgs {
   int* low;              // the lowest column index of every subtile
   int* redo;             // null, or the rows given up (see Redo) after
   int budget;            // this many subtiles
-  int from;              // Redo::from, and what else the kernels behind need to run
-  const FastGuard* guard;
+  int from;              // Redo::from
+  const FastGuard* guard;   // the fast kernel's, null: the direct one is behind
   float limit;
+  uint4* apk;               // its columns (FastPackArgs)
+  int64_t N16;
 };
 hipError_t launch_near(const NearArgs& a, hipStream_t s);
 
@@ -494,7 +496,6 @@ struct FastPackArgs {
   float* eb;          // sum: b per column
   int E;              // FAST_SUMV: signal columns of b (2..4)
   SortedCols so;      // ordered path: columns in the order's places, N16 a multiple of 64
-  Redo redo;          // FAST_MIN, FAST_KNN: whether to do anything
 };
 // The box of both clouds into the guard (knots: and the sample's quantiles); then the
 // packed columns.

@@ -202,9 +202,9 @@ def test_ordered_log_sums_of_masked_columns(ctx, low):
 
 
 # with the order and the all-pairs kernels' scratch behind it, the order
-# alone (the kernels behind pack 100 bytes a column), points in place (more rows than the
+# alone (the kernels behind pack 80 bytes a column), points in place (more rows than the
 # order has room for)
-@pytest.mark.parametrize("M,N,K,fits", [(1500, 20000, 4, True), (1500, 300000, 10, False), (2200000, 3000, 4, False),
+@pytest.mark.parametrize("M,N,K,fits", [(1500, 20000, 4, True), (1500, 450000, 10, False), (2200000, 3000, 4, False),
                                         (2200000, 3000, 1, False)])
 def test_small_scratch_lists(ctx, M, N, K, fits):
     """The no-allocation entry point keeps taking calls whose scratch has no room for all of the order's."""
