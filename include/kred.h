@@ -182,12 +182,12 @@ kred_status kred_destroy(kred_ctx* ctx);
  * distance's sums and extremes always use the fp64 contraction.  ARGKMIN /
  * KMIN rank in fp32 and re-rank the merged candidates by their direct-form
  * distance (KMIN values are the distances of the returned points).  D <= 4 with
- * col_blocks = 0 and neither FAST nor DIRECT: large calls first order both
- * clouds in space (scratch grows by about 16 (M + N) + 20 N bytes).  The lists
- * (also MIN / ARGMIN of the distance) are then found among near columns only,
- * in the direct form; the Gaussian sums, GAUSS_GRADX, and the Gaussian and
- * Sinkhorn LSE leave out column groups whose whole weight in a row stays below
- * 2^-30 sum_j |k_ij b_j| (LSE: of the sum).  Inputs
+ * col_blocks = 0 and without DIRECT: large calls first order both clouds in
+ * space (scratch grows by about 16 (M + N) + 20 N bytes).  The lists (also MIN /
+ * ARGMIN of the distance; not with FAST) are then found among near columns only,
+ * in the direct form, unless the order helps too few rows; the Gaussian sums,
+ * GAUSS_GRADX, and the Gaussian and Sinkhorn LSE leave out column groups whose
+ * whole weight in a row stays below 2^-30 sum_j |k_ij b_j| (LSE: of the sum).  Inputs
  * must be finite (NaN or Inf in x, y or b gives an undefined result).
  * Edge cases: M = 0 returns KRED_OK and touches nothing.  N = 0 writes zeros
  * (SUM), -infinity (LSE, MAX), +infinity (MIN) or -1 (ARGMIN, ARGMAX) and

@@ -8,18 +8,19 @@
 // order: first the subtile at the rows' own place on the curve, then, nearest
 // first, those whose bounding box comes as near to some row as that row's K-th
 // nearest so far (boxes of 64 subtiles, then of one: a lane tests a box), each
-// for the rows that need it.  On a mixture of normals a row meets 6 subtiles
-// and a wave of 16 rows 16, at most 34; tested against the rows' common box and
-// the farthest K-th alone, a wave of outliers met 830 and set the time.
-// 200 003 x 250 000 points, K = 10: 0.40 ms in all; 10^6 x 10^6: 107 -> 2.2 ms.
+// for the rows that need it.  On a mixture of normals a row meets 6 subtiles;
+// tested against the rows' common box and the farthest K-th alone, a wave of
+// outliers met 830 and set the time.  Waves that look at too many subtiles give
+// their rows up (see Redo).
+// 200 003 x 250 000 points, K = 10: 0.37 ms in all; 10^6 x 10^6: 107 -> 2.2 ms.
 //
 // In a subtile a lane is a column: 64 distances to a row in the direct form
 // sum_d (x_d - y_d)^2, the form the result is defined by, so there is nothing
 // to re-rank and no limit on the data's extent.  A row's list is one sorted
 // (distance, index) entry per lane, so an insertion is a compare, a count and
 // a shift by one lane whatever K is (64 nearest of 200 003 x 250 000: 172 -> 1.0
-// ms), and the test that keeps columns out uses the exact K-th distance.  Equal distances keep the lower index, whatever the
-// order the columns come in.
+// ms), and the test that keeps columns out uses the exact K-th distance.  Equal
+// distances keep the lower index, whatever the order the columns come in.
 #include "k_fast_slots.h"
 
 #include <cfloat>
@@ -117,7 +118,7 @@ __device__ __forceinline__ void near_rows(const NearArgs& a, int wave, int budge
   const int rows = (int)min((int64_t)R, a.M - r0);
   const int K = a.K;
 
-  // lane l holds row l mod 16 (a missing row repeats the last); the box of all
+  // lane l holds row l mod R (a missing row repeats the last); the box of all
   const int64_t mine = a.so.order_x[r0 + min(lane & (R - 1), rows - 1)];
   float xv[D], lo[D], hi[D];
 #pragma unroll

@@ -545,7 +545,7 @@ struct WideArgs {
   int NX;                     // WIDE_SUM4: 1 or 4 signal columns; WIDE_VJP: wide_dots(Ec)
   int64_t M, N, NP;           // NP: N padded to a multiple of 128
   int C;
-  int64_t jpb;                // a multiple of 64
+  int64_t jpb;                // a multiple of 128, the kernel's column tile
   const float* x;
   const float* y;
   const float* b;             // N x E
