@@ -341,8 +341,9 @@ constexpr int fast_waves(int EPI, int KL, bool sorted) {
 // The subtiles of a chunk of 1024 are tested together, each thread four, after
 // one box for every 64, and the ones that matter go into a list in LDS, which
 // the streaming loop follows four to a tile.
-// 10^6 x 10^6 on a mixture of 8 normals (std 0.05, sigma 0.05): sum 98 -> 32 ms,
-// gradient 160 -> 51, log-sum-exp 112 -> 32; on the unit cube at sigma 0.1: 98 ->
+// 10^6 x 10^6 on a mixture of 8 normals (std 0.05, sigma 0.05): sum 97 -> 27 ms,
+// gradient 159 -> 42 on the benchmark's, 27 to 36 and 42 to 54 with other centres (34% of the
+// pairs evaluated at 36), log-sum-exp 112 -> 32; on the unit cube at sigma 0.1: 98 ->
 // 89, 162 -> 142, 113 -> 86.
 template <int EPI, int RB, bool KV = false, int KL = 1, bool SORT = false>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(fast_waves(EPI, KL, SORT))))

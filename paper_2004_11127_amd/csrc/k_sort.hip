@@ -11,11 +11,11 @@
 // Both clouds go through the same launches (blocks of one cloud, then of the
 // other), and the first histogram is taken where the keys are made.  Latency
 // and launches bound it, so up to 2^17 points a cloud every scatter adds up the blocks
-// before its own by itself, and for the sums (the lists up to 2^16 at D <= 2, 2^15 at D = 3, 2^14 at D = 4) the keys
-// have 16 bits and two passes: four launches instead of nine.  us, nine launches and
-// four: 10 nearest of 6000 x 7000 points, D = 2 91 -> 72; of a mixture at D = 3, 32 000 x
-// 32 000 129 -> 117, at 65 000 181 -> 184 and at D = 4 258 -> 309 (too many points a cell); sum
-// of 10^5 x 10^5 whose order is of no use 1183 -> 1173.  (Histograms of the later passes by
+// before its own by itself, and where 16 bits leave few points a cell (D <= 2, the lists
+// of 2^15 points at D = 3 and of 2^14 at D = 4) two passes do: four launches instead of
+// nine.  us, nine launches and four: 10 nearest of 6000 x 7000 points, D = 2 91 -> 72; of a
+// mixture at D = 3, 32 000 x 32 000 129 -> 117, at 65 000 181 -> 184 and at D = 4 258 ->
+// 309; gradient of a mixture at D = 3, about 10^5 x 10^5, 3230 -> 3290.  (Histograms of the later passes by
 // atomics in the scatter before: 60 us slower at 200 000 points.)  (A
 // library sort would clear its counters with memory-set nodes, which a caller
 // that captures the reduction in a graph must not get.)
@@ -330,8 +330,8 @@ hipError_t launch_sort(SortArgs& a, void* scratch, hipStream_t s) {
   a.totals = reinterpret_cast<int*>(p + 4 * up(n * 4) + up(nb * 256 * 4));
   a.key0 = k0;
   a.small = a.M <= kSortSmall && a.N <= kSortSmall;
-  // (the lists, whose rows look at single cells, want fewer points in one)
-  a.passes = a.small && (!a.always || std::max(a.M, a.N) <= (a.D <= 2 ? 65536 : a.D == 3 ? 32768 : 16384)) ? 2 : 3;
+  const int64_t n2 = a.D <= 2 ? (a.always ? 65536 : kSortSmall) : !a.always ? 0 : a.D == 3 ? 32768 : 16384;
+  a.passes = a.small && std::max(a.M, a.N) <= n2 ? 2 : 3;
   const dim3 grid((unsigned)nb), block(256);
   hipLaunchKernelGGL(sort_keys_kernel, grid, block, 0, s, a);
   unsigned int* key[2] = {k0, k1};

@@ -96,13 +96,13 @@ __device__ __forceinline__ FastFrame fast_frame(const FastGuard* g, int D, float
   return f;
 }
 // Squared diagonal, in log2 units, of the clouds' bulk: along each coordinate the
-// span of 27 / 32 of the sample, scaled to the whole (a uniform cloud's box).  Some
+// span of 31 / 32 of the sample, scaled to the whole (a uniform cloud's box).  Some
 // far points stretch the box and not this.
 __device__ __forceinline__ float bulk_range(const FastGuard* g, int D, float scale) {
   float r = 0.0f;
   for (int d = 0; d < kFastMaxD; ++d)
     if (d < D) {
-      const float h = (g->knot[d][29] - g->knot[d][2]) * (32.0f / 27.0f) * scale;
+      const float h = (g->knot[d][kKnots - 1] - g->knot[d][0]) * (32.0f / 31.0f) * scale;
       r = __builtin_fmaf(h, h, r);
     }
   return r;

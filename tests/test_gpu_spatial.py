@@ -108,7 +108,7 @@ def _clouds(rng, M, N, D, data):
 
 
 def _bulk(x, y, d):
-    """The span of 27 / 32 of the device's sample along d, scaled to the whole: 128 points of each cloud, one
+    """The span of 31 / 32 of the device's sample along d, scaled to the whole: 128 points of each cloud, one
     from a pseudo-random place in each 128th."""
     v = []
     for p in (x, y):
@@ -117,7 +117,7 @@ def _bulk(x, y, d):
             at, end = n * u // 128, n * (u + 1) // 128
             v.append(p[min(at + (((t + 1) * 2654435761 & 0xFFFFFFFF) >> 8) % max(end - at, 1), n - 1), d])
     q = np.sort(np.array(v))[4::8]
-    return float(q[29] - q[2]) * 32 / 27
+    return float(q[31] - q[0]) * 32 / 31
 
 
 def _ordered(x, y, c):
