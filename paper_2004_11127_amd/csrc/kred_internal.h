@@ -562,8 +562,9 @@ struct WideArgs {
   float* out;
   float* part;
   int accumulate;             // WIDE_VJP with C = 1: add to out
+  double pr, pc, wr, wc, half;   // set by launch_wide: how the operands are scaled
 };
-hipError_t launch_wide(const WideArgs& a, hipStream_t s);
+hipError_t launch_wide(WideArgs& a, hipStream_t s);
 int wide_chunks(int D);
 int wide_dots(int Ec);
 // The largest box it takes (see fast_frame).  KRED_FLAG_FAST: as far as the bound in
