@@ -26,7 +26,7 @@ def test_sums_of_more_items_than_a_launch_holds():
 @pytest.mark.parametrize("D,ordered", [(3, True), (4, False)])
 def test_sums_do_not_order_points_that_no_order_can_help(D, ordered):
     """From 10^10 pairs on sums may order their points (16 bytes a point).  At these sizes the rule
-    asks for a range of 317 log2 units at D = 3 and of 900 at D = 4, where the matrix-core path's box
+    asks for a range of about 270 log2 units at D = 3 and of 700 at D = 4, where the matrix-core path's box
     spans at most 4 * 128, times (32 / 31)^2 for the bulk's."""
     cols = 90_001
     rows = 10 ** 10 // cols

@@ -126,8 +126,8 @@ def _ordered(x, y, c):
     (M, D), N = x.shape, len(y)
     half = (np.maximum(x.max(0), y.max(0)) - np.minimum(x.min(0), y.min(0))) / 2
     f = (256 / M) ** (1 / D) + (64 / N) ** (1 / D)
-    return (M * N >= 1e10 and f < 0.6 and c * (half ** 2).sum() <= fast_limit(D, False)
-            and c * sum(_bulk(x, y, d) ** 2 for d in range(D)) >= 45 / (0.6 - f) ** 2)
+    return (M * N >= 1e10 and f < 0.63 and c * (half ** 2).sum() <= fast_limit(D, False)
+            and c * sum(_bulk(x, y, d) ** 2 for d in range(D)) >= 45 / (0.63 - f) ** 2)
 
 
 def test_far_points_do_not_make_an_order_useful():
