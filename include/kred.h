@@ -183,7 +183,8 @@ kred_status kred_destroy(kred_ctx* ctx);
  * KMIN rank in fp32 and re-rank the merged candidates by their direct-form
  * distance (KMIN values are the distances of the returned points).  D <= 4 with
  * col_blocks = 0 and without DIRECT: large calls first order both clouds in
- * space (scratch grows by about 16 (M + N) + 20 N bytes).  The lists (also MIN /
+ * space (scratch grows by about 20 (M + N) + 20 N bytes, or 4 M + 80 N if that
+ * is more and the call is for lists).  The lists (also MIN /
  * ARGMIN of the distance; not with FAST) are then found among near columns only,
  * in the direct form, unless the order helps too few rows; the Gaussian sums,
  * GAUSS_GRADX, and the Gaussian and Sinkhorn LSE leave out column groups whose

@@ -379,3 +379,27 @@ def test_time_of_lists_that_the_order_does_not_help(ctx):
     px, py = dev(x), dev(y)
     t2 = _us(lambda: ctx.run("sqdist", "argkmin", px, py, K=10))
     assert t2 <= 2 * plain, (t2, plain)
+
+
+@pytest.mark.parametrize("some", [False, True])
+def test_way_back_repeats_under_graph_replay(ctx, some):
+    """Every replay counts its own given up rows: all of them, or some among others."""
+    import torch
+    rng = np.random.default_rng(9)
+    y = dev(_shell(rng, 20001, 12))
+    x = rng.integers(-1, 2, (16500, 3)).astype(np.float32)
+    if some:
+        x[np.arange(16500) % 977 != 5] += 9
+    x = dev(x)
+    want = ctx.run("sqdist", "argkmin", x, y, K=10)
+    out = torch.empty_like(want)
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        ctx.run("sqdist", "argkmin", x, y, out=out, K=10, stream=torch.cuda.current_stream())
+    for _ in range(4):
+        out.zero_()
+        ctx.run("sqdist", "argkmin", y, x, K=3)      # other work on the same scratch
+        torch.cuda.synchronize()
+        g.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(out, want)
